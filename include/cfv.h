@@ -168,7 +168,9 @@ cfv_status cfv_vjp(cfv_ctx* ctx, const double* U, const double* w, double* gU, d
  * time step set by the CFL number (Sections 2.1 and 4.1): diag[c] = V_c/dt_c
  * = sum over the six faces of s_f |S_f| / cfl, s_f the Rusanov speed of the
  * face (max of |v_n| + c_f on both reconstructed sides and c_h).  diag:
- * device [ncells].  CFV_ERR_ARG unless cfl > 0.  Asynchronous. */
+ * device [ncells]; it may overlap U (which is read before it is written, and
+ * then holds diag there).  CFV_ERR_ARG unless cfl > 0.  Asynchronous; an
+ * overlap uses the context's workspace. */
 cfv_status cfv_local_dt(cfv_ctx* ctx, const double* U, double cfl, double* diag, hipStream_t s);
 
 /* Non-physical state check (the face-state positivity condition of the

@@ -419,10 +419,15 @@ cfv_status cfv_local_dt(cfv_ctx* c, const double* U, double cfl, double* diag, h
   if (cfv_status st = check_ctx(c)) return st;
   if (!U || !diag) return fail(CFV_ERR_ARG, "null state or output");
   if (!(cfl > 0.0)) return fail(CFV_ERR_ARG, "cfl must be positive");
+  const int64_t nc = c->grid->g.ncells;
+  // the march writes a tile's cells while others still read U: a result over
+  // U's own memory goes through the workspace
+  const bool over = diag < U + 9 * nc && U < diag + nc;
   cfv::MarchArgs a{c->dev(), U, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
-  a.D = diag;
+  a.D = over ? c->W : diag;
   a.cfl = cfl;
   CFV_HIP(cfv::launch_fused(a, c->march_chunk(false), cfv::kOutSpeeds, s, c->tm()));
+  if (over) CFV_HIP(hipMemcpyAsync(diag, c->W, size_t(nc) * sizeof(double), hipMemcpyDeviceToDevice, s));
   return CFV_OK;
 }
 
