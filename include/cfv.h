@@ -243,7 +243,8 @@ cfv_status cfv_axpby(cfv_ctx* ctx, int64_t n, double a, const double* x, double 
  * iteration's Hessenberg column, for the Givens least squares, with the next
  * iteration already launched, and synchronises s before it returns.  The
  * Krylov workspace ((m+1) state vectors) is owned by the context and grown on
- * first use.
+ * first use.  CFV_ERR_NONPHYSICAL when rhs or a Krylov scalar is not finite;
+ * x is then the last complete cycle's iterate (zero in the first cycle).
  * This is the linear solve of the implicit backward-Euler pseudo-time step
  * of Section 2.1. */
 cfv_status cfv_solve(cfv_ctx* ctx, const double* U, const double* diag, const double* rhs, int32_t transpose,

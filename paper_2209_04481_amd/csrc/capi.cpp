@@ -557,10 +557,11 @@ static cfv_status apply_jacobian(cfv_ctx* c, const double* U, int transpose, con
 // GMRES cycles of cfv_solve (arguments checked, workspace there).  The host
 // reads column j of H while the device already runs step j + 1, so it never
 // leaves the device idle; a stop at column j leaves one step more than needed,
-// whose vectors are not used.
+// whose vectors are not used.  written: set once a cycle's update of x is
+// enqueued.
 static cfv_status solve_cycles(cfv_ctx* c, const double* U, const double* diag, const double* rhs, int32_t transpose,
                                int32_t m, int32_t max_restarts, double rtol, double* x, double* hist, int32_t hist_len,
-                               int32_t* iters, double* final_rel, hipStream_t s) {
+                               int32_t* iters, double* final_rel, bool* written, hipStream_t s) {
   const int64_t nc = c->grid->g.ncells, n = 9 * nc;
   double* V = c->kry_V;
   double* w = c->kry_w;
@@ -668,6 +669,7 @@ static cfv_status solve_cycles(cfv_ctx* c, const double* U, const double* diag, 
     Ok.k = kdone;
     CFV_HIP(cfv::launch_krylov_put(K, Ok, c->kry_sys, c->kry_out, s));
     CFV_HIP(cfv::launch_krylov_combine(c->kry_sys, c->kry_out, nullptr, K.nb, s));
+    *written = true;
     CFV_HIP(hipStreamSynchronize(s));
     if (stop) break;
   }
@@ -683,8 +685,11 @@ cfv_status cfv_solve(cfv_ctx* c, const double* U, const double* diag, const doub
   if (!U || !diag || !rhs || !x) return fail(CFV_ERR_ARG, "null argument");
   if (m < 1 || m > 200 || max_restarts < 0) return fail(CFV_ERR_ARG, "need 1 <= m <= 200 and max_restarts >= 0");
   if (cfv_status st = ensure_krylov(c, m)) return st;
+  bool written = false;
   const cfv_status st = solve_cycles(c, U, diag, rhs, transpose, m, max_restarts, rtol, x, hist, hist_len, iters,
-                                     final_rel, s);
+                                     final_rel, &written, s);
+  // a solve that fails in its first cycle leaves the zero it starts from
+  if (st != CFV_OK && !written) (void)hipMemsetAsync(x, 0, size_t(9) * c->grid->g.ncells * sizeof(double), s);
   // steps enqueued ahead of a stop or a failure read the caller's arrays:
   // nothing is left running on them
   CFV_HIP(hipStreamSynchronize(s));

@@ -39,3 +39,25 @@ def test_local_dt_over_the_state_it_reads(N, Nr):
         assert torch.equal(got, ref), at
         V.view(-1)[at:at + nc] = U.view(-1)[at:at + nc]
         assert torch.equal(V, U), at
+
+
+@pytest.mark.parametrize("transpose", [False, True])
+@pytest.mark.parametrize("bad", ["rhs", "state", "diagonal"])
+def test_a_solve_that_fails_leaves_the_zero_it_starts_from(bad, transpose):
+    """A NaN in the right-hand side, the state or the diagonal ends the solve
+    in its first cycle: x is then zero, whatever the memory held."""
+    from paper_2209_04481_amd.binding import CfvNonPhysical
+    ctx, U = shell(4, 6)
+    b = torch.randn(U.shape, dtype=torch.float64, device="cuda", generator=torch.Generator(device="cuda").manual_seed(3))
+    D = ctx.local_dt(U, 2.0)
+    {"rhs": b, "state": U, "diagonal": D}[bad].view(-1)[11] = float("nan")
+    x = torch.full_like(U, 7.0)
+    print(f"case: solve 4 x 6, NaN in the {bad}, transpose {transpose}", flush=True)
+    with pytest.raises(CfvNonPhysical):
+        ctx.solve(U, D, b, transpose=transpose, m=5, max_restarts=1, out=x)
+    assert not bool(x.any())
+    # and the context solves again
+    ctx2, U2 = shell(4, 6)
+    b2 = torch.ones_like(U2)
+    y, hist = ctx.solve(U2, ctx2.local_dt(U2, 2.0), b2, transpose=transpose, m=5)
+    assert bool(torch.isfinite(y).all()) and len(hist) == 5
