@@ -87,7 +87,17 @@ struct AState {
   double ring[7];  // the lane's share of its slot's 27 values
 };
 
-struct AdjWG {
+// Narrow: for shells whose panels end in tiles one or two columns wide.  The
+// lanes of such a tile that would have no cell repeat its columns, lane by
+// lane the same values to the same places, so that all 64 lanes of its
+// wavefronts work.  With 4 or 8 of them working, a layer took 35 us instead of
+// 20 wherever no fuller tile ran in the same shader engine: the wavefronts
+// wait for issue (SQ_WAIT_INST_ANY twice as high, no instruction cache
+// misses), those of a tile with one wavefront do not.  An instance of its own:
+// the column from the cell instead of the lane number costs full tiles 1%
+// (48 x 120 954 and 967 us).
+template <bool Narrow>
+struct AdjMarch {
   // LDS: planes of primitives and weights of layer k (18 x 18 positions, the
   // tile and a ring), the column centroid sums (a plane of 3), the cells'
   // angular face-centroid offsets per unit rs_k (12 rows of 256), and per
@@ -98,6 +108,7 @@ struct AdjWG {
   static constexpr int kP = 0, kW = kP + 9 * kPlane, kCs = kW + 9 * kPlane, kFe = kCs + 3 * kPlane,
                        kX = kFe + 12 * kNT, kLds = kX + 36 * kRow;
   __host__ __device__ static int x_at(int q, int v) { return kX + (9 * q + v) * kRow; }
+  __host__ __device__ static int tile_i(const AState& st, int t) { return Narrow ? st.i % kTI : t % kTI; }
 
   __host__ __device__ static void load9(const double* a, int64_t nc, int64_t c, double q[9]) {
 #pragma unroll
@@ -112,9 +123,9 @@ struct AdjWG {
   __host__ __device__ static void init(const AdjArgs& a, const TileMap& tm, AState& st, int t, double* lds) {
     const Shape& g = a.d.g;
     const GeomRef& G = a.d.G;
-    const int ti = t % kTI, tj = t / kTI;
     const int tiL = (g.N - tm.i0 < kTI ? g.N - tm.i0 : kTI) - 1;
     const int tjL = (g.N - tm.j0 < kTJ ? g.N - tm.j0 : kTJ) - 1;
+    const int ti = Narrow && tiL < 2 ? t % kTI & tiL : t % kTI, tj = t / kTI;
     st.p = tm.p;
     st.j = tm.j0 + tj;
     st.i = tm.i0 + ti;
@@ -253,7 +264,7 @@ struct AdjWG {
   __host__ __device__ static void publish(const AdjArgs& a, const TileMap& tm, AState& st, int t, double* lds) {
     const Shape& g = a.d.g;
     if (st.act) {
-      const int me = plane_pos(t % kTI, t / kTI);
+      const int me = plane_pos(tile_i(st, t), t / kTI);
 #pragma unroll
       for (int v = 0; v < 9; ++v) {
         lds[kP + v * kPlane + me] = st.P0[v];
@@ -283,7 +294,7 @@ struct AdjWG {
   __host__ __device__ static void publish_states(const AdjArgs& a, AState& st, int t, int k, double* lds) {
     if (!st.act) return;
     const GeomRef& G = a.d.G;
-    const int me = plane_pos(t % kTI, t / kTI);
+    const int me = plane_pos(tile_i(st, t), t / kTI);
     const double r0 = radius_uniform(G, k), r1 = radius_uniform(G, k + 1), rs = 0.125 * (r0 + r1);
     double P[9], q9[9];
 #pragma unroll
@@ -328,7 +339,7 @@ struct AdjWG {
     if (!st.act) return;
     const Shape& g = a.d.g;
     const GeomRef& G = a.d.G;
-    const int ti = t % kTI, tj = t / kTI, me = plane_pos(ti, tj);
+    const int ti = tile_i(st, t), tj = t / kTI, me = plane_pos(ti, tj);
     const int tiL = (g.N - tm.i0 < kTI ? g.N - tm.i0 : kTI) - 1;
     const int tjL = (g.N - tm.j0 < kTJ ? g.N - tm.j0 : kTJ) - 1;
     const double r0 = radius_uniform(G, k), r1 = radius_uniform(G, k + 1);
@@ -396,7 +407,7 @@ struct AdjWG {
     if (!st.act) return;
     const Shape& g = a.d.g;
     const GeomRef& G = a.d.G;
-    const int ti = t % kTI, tj = t / kTI, me = plane_pos(ti, tj);
+    const int ti = tile_i(st, t), tj = t / kTI, me = plane_pos(ti, tj);
     const double r0 = radius_uniform(G, k), r1 = radius_uniform(G, k + 1);
     const double rs = 0.125 * (r0 + r1);
     const V3 cc = centroid_sum(lds, me), xc = rs * cc;
@@ -418,6 +429,7 @@ struct AdjWG {
     }
     const LsqWeights Lw(dx);
     double up[9];
+    const bool first = !Narrow || t % kTI == ti;  // the others add the same to the same entries
     const int64_t seam0 = k == tm.k0 && k > 0 ? int64_t(k / a.kc - 1) * 18 * g.nb : 0;
     const int64_t seam1 = k == tm.k1 - 1 && k + 1 < g.Nr ? int64_t(k / a.kc) * 18 * g.nb : 0;
 #pragma unroll
@@ -435,15 +447,15 @@ struct AdjWG {
       const double own = st.Pb[v] + pb;
 #pragma unroll
       for (int q = 0; q < 4; ++q) lds[x_at(q, v) + t] = o[2 + q];
-      if (k == 0)
-        gst(a.Gg, v * g.nb + st.col, gld(a.Gg, v * g.nb + st.col) + o[0]);
-      else if (k == tm.k0)
+      if (k == 0) {
+        if (first) gst(a.Gg, v * g.nb + st.col, gld(a.Gg, v * g.nb + st.col) + o[0]);
+      } else if (k == tm.k0)
         gst(a.S, seam0 + v * g.nb + st.col, o[0]);
       else
         st.acc[v] += o[0];  // of layer k - 1, now complete
-      if (k == g.Nr - 1)
-        gst(a.Gg, (9 + v) * g.nb + st.col, gld(a.Gg, (9 + v) * g.nb + st.col) + o[1]);
-      else if (k == tm.k1 - 1)
+      if (k == g.Nr - 1) {
+        if (first) gst(a.Gg, (9 + v) * g.nb + st.col, gld(a.Gg, (9 + v) * g.nb + st.col) + o[1]);
+      } else if (k == tm.k1 - 1)
         gst(a.S, seam1 + (9 + v) * g.nb + st.col, o[1]);
       up[v] = o[1];
       st.Pb[v] = own;
@@ -547,7 +559,7 @@ struct AdjWG {
     double Ub[9];
     prim_adjoint_prims(q, st.acc, Ub, a.d.pr.gamma);
     const double vol = (r1 * r1 * r1 - r0 * r0 * r0) * st.om * (1.0 / 3.0);
-    gravity_adjoint((0.125 * (r0 + r1)) * centroid_sum(lds, plane_pos(t % kTI, t / kTI)), vol, a.d.pr.G, wg, Ub);
+    gravity_adjoint((0.125 * (r0 + r1)) * centroid_sum(lds, plane_pos(tile_i(st, t), t / kTI)), vol, a.d.pr.G, wg, Ub);
     const bool raw = st.edge || kk == 0 || kk == g.Nr - 1 || kk == tm.k0 || kk == tm.k1 - 1;
     const int64_t c = cell_index(g, st.p, kk, st.j, st.i);
 #pragma unroll
@@ -559,7 +571,7 @@ struct AdjWG {
   __host__ __device__ static void gather(const AdjArgs& a, const TileMap& tm, AState& st, int t, int k,
                                          const double* lds) {
     const Shape& g = a.d.g;
-    const int ti = t % kTI, tj = t / kTI;
+    const int ti = tile_i(st, t), tj = t / kTI;
     const int tiL = (g.N - tm.i0 < kTI ? g.N - tm.i0 : kTI) - 1;
     const int tjL = (g.N - tm.j0 < kTJ ? g.N - tm.j0 : kTJ) - 1;
     if (t >= 2 * kEdgeSlots && t < 3 * kEdgeSlots) {
@@ -596,6 +608,8 @@ struct AdjWG {
     }
   }
 };
+
+using AdjWG = AdjMarch<true>;  // whichever the shell (the host emulation)
 
 // Per boundary column, side and input a of the boundary law (0..8 the cell's
 // primitives, 9 the B_r map): the ghost state's adjoint through the law, one

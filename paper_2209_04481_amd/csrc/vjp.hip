@@ -104,8 +104,10 @@ __global__ __launch_bounds__(kVBlock) void gather_kernel(DevGrid d, const double
 // ------------------------------------------------------------- the march
 // One tile and chunk per workgroup, items dealt to the XCDs in contiguous
 // eighths (neighbouring tiles share an L2).
+template <bool Narrow>
 __global__ __launch_bounds__(kNT, 1) void adjoint_march_kernel(AdjArgs, int64_t total) {
-  __shared__ double lds[AdjWG::kLds];
+  using WG = AdjMarch<Narrow>;
+  __shared__ double lds[WG::kLds];
   const AdjArgs& a0 = constant_args(&first_kernel_arg<AdjArgs>());
   const int64_t per = (total + 7) / 8;
   const int64_t item = int64_t(blockIdx.x % 8) * per + blockIdx.x / 8;
@@ -114,24 +116,24 @@ __global__ __launch_bounds__(kNT, 1) void adjoint_march_kernel(AdjArgs, int64_t 
   TileMap tm;
   tile_of_logical(a0.d.g, item, tm, a0.kc);
   AState st;
-  AdjWG::init(a0, tm, st, t, lds);
-  AdjWG::fetch_ring(a0, st, t, tm.k0);
-  AdjWG::publish(a0, tm, st, t, lds);
-  AdjWG::publish_states(a0, st, t, tm.k0, lds);
+  WG::init(a0, tm, st, t, lds);
+  WG::fetch_ring(a0, st, t, tm.k0);
+  WG::publish(a0, tm, st, t, lds);
+  WG::publish_states(a0, st, t, tm.k0, lds);
   for (int k = tm.k0;;) {
     const AdjArgs& a = per_layer(a0);
     const bool more = k + 1 < tm.k1;
     __syncthreads();
-    AdjWG::faces(a, tm, st, lane_here(t), k, lds);
+    WG::faces(a, tm, st, lane_here(t), k, lds);
     __syncthreads();
-    AdjWG::gradient(a, tm, st, lane_here(t), k, lds);
+    WG::gradient(a, tm, st, lane_here(t), k, lds);
     __syncthreads();
-    if (more) AdjWG::publish(a, tm, st, lane_here(t), lds);
-    AdjWG::gather(a, tm, st, lane_here(t), k, lds);
+    if (more) WG::publish(a, tm, st, lane_here(t), lds);
+    WG::gather(a, tm, st, lane_here(t), k, lds);
     if (!more) break;
     __syncthreads();
     ++k;
-    AdjWG::publish_states(a, st, lane_here(t), k, lds);
+    WG::publish_states(a, st, lane_here(t), k, lds);
   }
 }
 
@@ -152,15 +154,16 @@ __global__ __launch_bounds__(kVBlock) void adjoint_finish_kernel(AdjArgs) {
 
 // Layers per chunk of the adjoint's march for a shell, or 0 where the
 // cell-centric passes are the better path.  A tile's layer takes a workgroup
-// 20-22 us (35 at N = 17 and 18) however many of its 256 lanes hold cells, and
+// 20-22 us however many of its 256 lanes hold cells, and
 // a chunk about one layer more; 256 consecutive cells take the cell-centric
 // passes about 45 us and those passes 55 us more of launches and tails.  So
 // tiles that divide a panel badly (N = 17 in four tiles of 16: 24 tiles for
 // 6.8 tiles of cells) or hardly fill one (N <= 6 with many layers) go cell by
-// cell.  In us, by the march and cell by cell: 17 x 60 322 and 207, 33 x 60 477
-// and 450, 6 x 200 175 and 161, 4 x 300 261 and 165; 32 x 60 235 and 386, 20 x 60
-// 214 and 231, 24 x 80 273 and 346, 16 x 40 82 and 138, 8 x 16 65 and 118.  (The
-// estimate is a few us out where both are near, 8 x 120 127 and 144.)
+// cell.  In us, by the march and cell by cell: 17 x 100 323 and 259, 33 x 60 475
+// and 449, 6 x 200 175 and 161, 4 x 300 261 and 165; 17 x 40 160 and 185, 49 x 60
+// 792 and 908, 32 x 60 235 and 386, 20 x 60 214 and 231, 24 x 80 273 and 346, 16 x
+// 40 82 and 138, 8 x 16 65 and 118.  (The estimate is a few us out where both are
+// near, 8 x 120 127 and 144, 17 x 60 218 and 204.)
 // (N < 4 too: the march's edge contributions, 576 values per tile and layer,
 // take the place of the cells' 54 face-state values.)
 int adjoint_march_chunk(const Shape& g, int cus) {
@@ -174,13 +177,29 @@ int adjoint_march_chunk(const Shape& g, int cus) {
   return march <= cells ? kc : 0;
 }
 
+// Whether narrow tiles' idle lanes repeat their columns (AdjMarch): where
+// wavefronts of four or eight lanes can run with no fuller tile in their
+// shader engine.  That is a panel of one full tile among four (N = 17, 18: 17 x
+// 40 234 us with idle lanes, 160 without), and a last round of items that
+// leaves compute units idle (49 x 60, 480 items on 256: 982 and 792; 65 x 60,
+// 750: 1,377 and 1,192).  Rounds that fill the device hide it (49 x 120, 768
+// items: 1,428 and 1,445; 34 x 60, one round: 457 and 460).
+static bool repeat_narrow_tiles(const Shape& g, int64_t items, int cus) {
+  if (g.N % kTI != 1 && g.N % kTI != 2) return false;
+  return g.N <= kTI + 2 || (items > cus && items % cus != 0);
+}
+
 // the adjoint and the passes after it, tile by tile
-static void launch_adjoint_march(const AdjArgs& a, hipStream_t s, KernelTimer* t) {
+static void launch_adjoint_march(const AdjArgs& a, int cus, hipStream_t s, KernelTimer* t) {
   const Shape& g = a.d.g;
   {
     TimedScope ts(t, "adjoint", s);
     const int64_t total = march_logical_blocks(g, a.kc);
-    hipLaunchKernelGGL(adjoint_march_kernel, dim3(unsigned((total + 7) / 8 * 8)), dim3(kNT), 0, s, a, total);
+    const dim3 grid(unsigned((total + 7) / 8 * 8));
+    if (repeat_narrow_tiles(g, total, cus))
+      hipLaunchKernelGGL(adjoint_march_kernel<true>, grid, dim3(kNT), 0, s, a, total);
+    else
+      hipLaunchKernelGGL(adjoint_march_kernel<false>, grid, dim3(kNT), 0, s, a, total);
   }
   {
     TimedScope ts(t, "adjoint_ghosts", s);
@@ -212,9 +231,9 @@ static void launch_adjoint_cells(const DevGrid& d, const double* U, const double
   hipLaunchKernelGGL(gather_kernel, grid, dim3(kVBlock), 0, s, d, U, w, A, gU);
 }
 
-// akc: layers per chunk of the adjoint's march (adjoint_march_chunk)
+// akc: layers per chunk of the adjoint's march (adjoint_march_chunk); cus: the device's compute units
 hipError_t launch_vjp(const DevGrid& d, const double* U, const double* w, double* gU, double* gbr, double* W,
-                      double* A, double* E, int kc, int akc, const int64_t* bw, int64_t nbw,
+                      double* A, double* E, int kc, int akc, int cus, const int64_t* bw, int64_t nbw,
                       hipStream_t s, KernelTimer* t) {
   const int64_t nc = d.g.ncells;
   // pass 1: the forward gradient march writes the primitives (rows 0..8 of
@@ -240,7 +259,7 @@ hipError_t launch_vjp(const DevGrid& d, const double* U, const double* w, double
   }
   if (hipError_t e = launch_march_grad(fa, kc, s, t)) return e;
   if (akc > 0)
-    launch_adjoint_march(a, s, t);
+    launch_adjoint_march(a, cus, s, t);
   else
     launch_adjoint_cells(d, U, w, gU, gbr, W, A, bw, nbw, s, t);
   return hipGetLastError();
