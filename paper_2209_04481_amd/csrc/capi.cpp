@@ -35,7 +35,7 @@ hipError_t launch_dots_noalloc(int64_t n, const double* V, int k, const double* 
 int dots_noalloc_max_vectors();
 hipError_t launch_axpby(int64_t n, double a, const double* x, double b, double* y, hipStream_t s);
 hipError_t launch_vjp(const DevGrid& d, const double* U, const double* w, double* gU, double* gbr, double* W,
-                      double* A, double* E, int kc, int akc, int cus, const int64_t* bw, int64_t nbw,
+                      double* A, double* E, int kc, bool ahead, int akc, int cus, const int64_t* bw, int64_t nbw,
                       hipStream_t s, KernelTimer* t);
 int adjoint_march_chunk(const Shape& g, int cus);
 int64_t vjp_workspace_doubles(const Shape& g);
@@ -139,6 +139,7 @@ struct cfv_ctx {
   int fused_chunk = cfv::kKC;  // the balanced choices for this grid and device
   int dual_chunk = cfv::kKC;
   int cus = 1;                // the device's compute units
+  bool face_ahead = true;     // cfv::face_states_ahead for the balanced chunk
   int adj_chunk = cfv::kKC;   // layers per chunk of the adjoint's march, 0: cell by cell (fixed per grid and device)
   int march_chunk(bool dual) const { return chunk ? chunk : dual ? dual_chunk : fused_chunk; }
   cfv::DevGrid dev() const {
@@ -156,7 +157,8 @@ struct cfv_ctx {
     return d;
   }
   hipError_t vjp(const double* U, const double* w, double* gU, double* gbr, hipStream_t s) {
-    return cfv::launch_vjp(dev(), U, w, gU, gbr, W, A, E, march_chunk(true), adj_chunk, cus, dbwin, nbwin, s, tm());
+    return cfv::launch_vjp(dev(), U, w, gU, gbr, W, A, E, march_chunk(true), face_ahead, adj_chunk, cus,
+                           dbwin, nbwin, s, tm());
   }
 };
 
@@ -303,6 +305,7 @@ cfv_status cfv_ctx_create(const cfv_grid* g, const cfv_params* prm, cfv_ctx** ou
     c->dual_chunk = cfv::balanced_chunk(dual_tiles, sh.Nr, cus);
     c->adj_chunk = cfv::adjoint_march_chunk(sh, cus);
     c->cus = cus;
+    c->face_ahead = cfv::face_states_ahead(sh, c->dual_chunk, cus);
   }
   c->pr.gamma = prm->gamma;
   c->pr.c_h = prm->c_h;

@@ -81,6 +81,19 @@ inline int balanced_chunk(int64_t tiles, int Nr, int64_t slots, int extra = 2) {
   return best;
 }
 
+// Whether the VJP's face-state pass loads its layers ahead (GradWG), at one
+// workgroup per CU, or not, at two.  It is for shells that fill tiles badly; by
+// the shell's own chunk length kc, whatever the caller's, since the two are not
+// the same bits.  Not ahead where the items take two rounds of one workgroup
+// per CU and one of two.  In us, the pass ahead and not: 33 x 160 (486 items on
+// 256 CUs) 371 and 280, 33 x 300 767 and 650; the whole VJP 49 x 60 (480) 904 and
+// 880.  Otherwise, the VJP in one round 33 x 40 324 and 331, 17 x 200 463 and 550
+// (its narrow tiles' idle lanes run along), in three 65 x 60 1,534 and 1,559.
+inline bool face_states_ahead(const Shape& g, int kc, int cus) {
+  const int64_t items = march_logical_blocks(g, kc);
+  return items <= cus || items > 2 * int64_t(cus);
+}
+
 // launch size: a multiple of 8 so that the XCD split is a bijection
 __host__ __device__ __forceinline__ int64_t march_blocks(const Shape& g, int kc) {
   return (march_logical_blocks(g, kc) + 7) / 8 * 8;
@@ -292,7 +305,11 @@ __host__ __device__ __forceinline__ bool ring_slot(const MarchArgs& a, const Til
   return true;
 }
 
-template <class T>
+// Ahead: layers are loaded through the layer below's gradients, for one
+// wavefront per SIMD, whose loads nothing else hides.  Without it they are
+// loaded where they are wanted, and lanes without a cell load and compute
+// nothing.
+template <class T, bool Ahead = true>
 struct GradWG {
   static constexpr int kTw = int(sizeof(T) / sizeof(double));
   // primitives plane (9 T per position), then the column centroid sums (3)
@@ -404,7 +421,7 @@ struct GradWG {
   __host__ __device__ static void publish(const MarchArgs& a, const TileMap& tm, GState<T>& st, int t, int k,
                                           double* lds) {
     const Shape& g = a.d.g;
-    if (st.rc0 >= 0) {  // rc0 >= 0: a ring lane with a neighbour
+    if (Ahead && st.rc0 >= 0) {  // rc0 >= 0: a ring lane with a neighbour
       if (k >= tm.k0) {
         arrived(a, st.ur);
         ring(a, tm, ring_slot_of(t), st.ur, lds);
@@ -413,14 +430,18 @@ struct GradWG {
         for (int v = 0; v < 9; ++v) fetch_ring(a, st, tm.k0, v);
       }
     }
-    if (k == first_layer(tm))
+    if (Ahead && k == first_layer(tm))
 #pragma unroll
       for (int v = 0; v < 9; ++v) fetch(a, st, k + 1, v);
     if (k + 1 >= 0 && k + 1 < g.Nr) {
-      arrived(a, st.u);
-      cons_to_prim(st.u, st.Pp, a.d.pr.gamma);
+      if constexpr (Ahead) {
+        arrived(a, st.u);
+        cons_to_prim(st.u, st.Pp, a.d.pr.gamma);
+      } else if (st.act) {
+        load_prims(a, cell_index(g, st.p, k + 1, st.j, st.i), st.Pp);
+      }
     }
-    if (k < tm.k0)
+    if (Ahead && k < tm.k0)
 #pragma unroll
       for (int v = 0; v < 9; ++v) fetch(a, st, k + 2, v);
     if (k < tm.k0) {
@@ -436,6 +457,12 @@ struct GradWG {
         const int64_t c = cell_index(g, st.p, k, st.j, st.i);
         for (int v = 0; v < 9; ++v) gst(a.P, v * g.ncells + c, val(st.P0[v]));
       }
+    }
+    if (!Ahead && st.rc0 >= 0 && k >= tm.k0) {
+      T ur[9];
+#pragma unroll
+      for (int v = 0; v < 9; ++v) ldT(a.U, a.Ud, v * g.ncells + st.rc0 + int64_t(k) * g.N * g.N, ur[v]);
+      ring(a, tm, ring_slot_of(t), ur, lds);
     }
   }
 
@@ -483,6 +510,7 @@ struct GradWG {
   template <int Mode = 0>
   __host__ __device__ static void compute(const MarchArgs& a, const TileMap& tm, GState<T>& st, int t, int k,
                                           double* lds) {
+    if (!Ahead && !st.act) return;
     const Shape& g = a.d.g;
     const GeomRef& G = a.d.G;
     const T* L = lds_as<T>(lds);
@@ -549,8 +577,8 @@ struct GradWG {
       // the next layers' loads, between the variables (the ring's in three
       // groups: all before the first variable 2.76 ms at 13.3M cells and 349 us
       // at 1.66M, one a variable 2.50 and 365, so 2.55 and 358)
-      fetch(a, st, k + 2, v);
-      if (v % 3 == 0 && st.rc0 >= 0)
+      if (Ahead) fetch(a, st, k + 2, v);
+      if (Ahead && v % 3 == 0 && st.rc0 >= 0)
 #pragma unroll
         for (int r = v; r < v + 3; ++r) fetch_ring(a, st, k + 1, r);
       T qn[6];
@@ -1039,8 +1067,8 @@ hipError_t launch_march(const MarchArgs& a, bool dual, int kc, hipStream_t s, Ke
 hipError_t launch_fused(const MarchArgs& a, int kc, int out, hipStream_t s, KernelTimer* t);
 // The VJP's forward pass (double): primitives into a.P, and the face states
 // into a.Q, or (a.Q null) the limited gradients into a.G, the ghost states
-// into a.Gs and the tile-edge cells' rows into a.E.
-hipError_t launch_march_grad(const MarchArgs& a, int kc, hipStream_t s, KernelTimer* t);
+// into a.Gs and the tile-edge cells' rows into a.E.  ahead: face_states_ahead.
+hipError_t launch_march_grad(const MarchArgs& a, int kc, bool ahead, hipStream_t s, KernelTimer* t);
 
 // Ensemble launch: n instances described by args[n] (device; null: one
 // instance, described by the kernel's second argument), with

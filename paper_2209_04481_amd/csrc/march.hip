@@ -30,9 +30,9 @@ namespace cfv {
 // --------------------------------------------------------------- device glue
 // One (tile, chunk) of each pass; the single-instance kernels run one per
 // workgroup, the ensemble kernels (ensemble.hip) loop over a queue of them.
-template <class T, int Mode = 0>
+template <class T, int Mode = 0, bool Ahead = true>
 __device__ __forceinline__ void grad_march_tile(const MarchArgs& a0, const TileMap& tm, double* lds) {
-  using WG = GradWG<T>;
+  using WG = GradWG<T, Ahead>;
   const int t = threadIdx.x;
   GState<T> st;
   WG::init(a0, tm, st, t, lds);
@@ -112,12 +112,13 @@ __device__ __forceinline__ int find_instance(const int64_t* __restrict__ off, in
   return lo;
 }
 
-// All are compiled for one wavefront per SIMD: the JVP passes hold the next
-// layer's loads in registers (474 and 512) and the flux pass 160 KB of LDS; the
-// VJP's forward pass, 377 registers, spills at two (2.26 against 1.52 ms at
-// 13.3M cells).
-template <class T, bool Flux, int Mode = 0>
-__global__ __launch_bounds__(kNT, 1) void march_ensemble_kernel(EnsembleLaunch e, MarchArgs) {
+// One wavefront per SIMD where the next layer's loads wait in registers: the
+// JVP passes (474 and 512 of them; the flux pass also has 160 KB of LDS) and
+// the VJP's forward passes (377; at two per SIMD they spill, 2.26 against 1.52
+// ms at 13.3M cells).  The forward pass without loads ahead: two, 160 B of
+// scratch a lane.
+template <class T, bool Flux, int Mode = 0, bool Ahead = true>
+__global__ __launch_bounds__(kNT, Ahead ? 1 : 2) void march_ensemble_kernel(EnsembleLaunch e, MarchArgs) {
   constexpr int kL = Flux ? FluxWG<T>::kLds : GradWG<T>::kLds;
   __shared__ double lds[kL];
   __shared__ int slot;
@@ -134,7 +135,7 @@ __global__ __launch_bounds__(kNT, 1) void march_ensemble_kernel(EnsembleLaunch e
     if (Flux)
       flux_march_tile<T>(a, tm, lds);
     else
-      grad_march_tile<T, Mode>(a, tm, lds);
+      grad_march_tile<T, Mode, Ahead>(a, tm, lds);
   }
 }
 
@@ -175,10 +176,12 @@ hipError_t launch_march(const MarchArgs& a, bool dual, int kc, hipStream_t s, Ke
   return hipGetLastError();
 }
 
-hipError_t launch_march_grad(const MarchArgs& a, int kc, hipStream_t s, KernelTimer* t) {
+hipError_t launch_march_grad(const MarchArgs& a, int kc, bool ahead, hipStream_t s, KernelTimer* t) {
   const EnsembleLaunch e = one_instance(a, kc);
   TimedScope ts(t, "grad_march_fwd", s);
-  if (a.Q)
+  if (a.Q && !ahead)
+    hipLaunchKernelGGL((march_ensemble_kernel<double, false, 1, false>), dim3(e.blocks), dim3(kNT), 0, s, e, a);
+  else if (a.Q)
     hipLaunchKernelGGL((march_ensemble_kernel<double, false, 1>), dim3(e.blocks), dim3(kNT), 0, s, e, a);
   else
     hipLaunchKernelGGL((march_ensemble_kernel<double, false, 2>), dim3(e.blocks), dim3(kNT), 0, s, e, a);

@@ -231,10 +231,12 @@ static void launch_adjoint_cells(const DevGrid& d, const double* U, const double
   hipLaunchKernelGGL(gather_kernel, grid, dim3(kVBlock), 0, s, d, U, w, A, gU);
 }
 
-// akc: layers per chunk of the adjoint's march (adjoint_march_chunk); cus: the device's compute units
+// kc: layers per chunk of the forward pass; ahead: face_states_ahead; akc: layers
+// per chunk of the adjoint's march (adjoint_march_chunk); cus: the device's
+// compute units
 hipError_t launch_vjp(const DevGrid& d, const double* U, const double* w, double* gU, double* gbr, double* W,
-                      double* A, double* E, int kc, int akc, int cus, const int64_t* bw, int64_t nbw,
-                      hipStream_t s, KernelTimer* t) {
+                      double* A, double* E, int kc, bool ahead, int akc, int cus, const int64_t* bw,
+                      int64_t nbw, hipStream_t s, KernelTimer* t) {
   const int64_t nc = d.g.ncells;
   // pass 1: the forward gradient march writes the primitives (rows 0..8 of
   // W), and the limited gradients (its other 27) with the ghost states and the
@@ -257,7 +259,7 @@ hipError_t launch_vjp(const DevGrid& d, const double* U, const double* w, double
   } else {
     fa.Q = A + int64_t(63) * nc;
   }
-  if (hipError_t e = launch_march_grad(fa, kc, s, t)) return e;
+  if (hipError_t e = launch_march_grad(fa, kc, ahead, s, t)) return e;
   if (akc > 0)
     launch_adjoint_march(a, cus, s, t);
   else
