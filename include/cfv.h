@@ -161,8 +161,10 @@ cfv_status cfv_jvp(cfv_ctx* ctx, const double* U, const double* v, const double*
  * of the implicit step and the sensitivity of an outer-boundary objective to
  * the magnetogram B_r map (Section 3.2).  w, gU: device [9][ncells].  A
  * hand-written reverse pass, the exact transpose of cfv_jvp's operator
- * (same branches).  Deterministic: no floating-point atomics.  Asynchronous;
- * uses the context's workspace. */
+ * (same branches).  Deterministic: no floating-point atomics.  gU may be the
+ * memory of w or U: such a call sums a cell's contributions in another order
+ * (equal to rounding), as does a device with another number of compute units.
+ * Asynchronous; uses the context's workspace. */
 cfv_status cfv_vjp(cfv_ctx* ctx, const double* U, const double* w, double* gU, double* gbr, hipStream_t s);
 /* Backward-Euler diagonal of the implicit pseudo-time step with a local
  * time step set by the CFL number (Sections 2.1 and 4.1): diag[c] = V_c/dt_c
@@ -241,10 +243,12 @@ cfv_status cfv_axpby(cfv_ctx* ctx, int64_t n, double a, const double* x, double 
  * the last relative residual.  x must not alias rhs.  The Arnoldi vectors,
  * dot products and updates stay on the device; the host waits for each
  * iteration's Hessenberg column, for the Givens least squares, with the next
- * iteration already launched, and synchronises s before it returns.  The
- * Krylov workspace ((m+1) state vectors) is owned by the context and grown on
- * first use.  CFV_ERR_NONPHYSICAL when rhs or a Krylov scalar is not finite;
- * x is then the last complete cycle's iterate (zero in the first cycle).
+ * iteration already launched (a solve that stops early at its tolerance has
+ * run one Jacobian product more than iters), and synchronises s before it
+ * returns.  The Krylov workspace ((m+1) state vectors) is owned by the context
+ * and grown on first use.  CFV_ERR_NONPHYSICAL when rhs or a Krylov scalar is
+ * not finite; x is then the last complete cycle's iterate (zero in the first
+ * cycle).
  * This is the linear solve of the implicit backward-Euler pseudo-time step
  * of Section 2.1. */
 cfv_status cfv_solve(cfv_ctx* ctx, const double* U, const double* diag, const double* rhs, int32_t transpose,
@@ -429,9 +433,10 @@ cfv_status cfv_timing_enable(cfv_ctx* ctx, int32_t on);
  * device's compute units: of the chunk counts, the one with the fewest
  * rounds of items times layers marched per item.  A chunk also marches the
  * layers on either side of it, so longer chunks move fewer bytes, shorter
- * ones give more work items on small grids.  Every output is bitwise the
- * same for every kc: each face flux is evaluated once from the same states,
- * and each cell sums its faces in a fixed order. */
+ * ones give more work items on small grids.  The VJP's adjoint march keeps a
+ * chunk length of its own.  Every output is bitwise the same for every kc:
+ * each face flux is evaluated once from the same states, and each cell sums
+ * its faces in a fixed order. */
 cfv_status cfv_set_chunk_layers(cfv_ctx* ctx, int32_t kc);
 /* Preconditioner of the context's GMRES solves (cfv_solve, and through it
  * cfv_be_step and cfv_steady): kind 0 none (the default; the step of

@@ -174,17 +174,6 @@ __host__ __device__ __forceinline__ void load_prims(const MarchArgs& a, int64_t 
   cons_to_prim(u, P, a.d.pr.gamma);
 }
 
-template <class T>
-__host__ __device__ __forceinline__ void load_grad(const MarchArgs& a, int64_t c, T Gr[27]) {
-  const int64_t nc = a.d.g.ncells;
-  for (int v = 0; v < 27; ++v) ldT(a.G, a.Gd, v * nc + c, Gr[v]);
-}
-
-template <class T>
-__host__ __device__ __forceinline__ void recon(const T P[9], const T Gr[27], V3 d, T q[9]) {
-  for (int v = 0; v < 9; ++v) q[v] = P[v] + (Gr[3 * v] * d.x + Gr[3 * v + 1] * d.y + Gr[3 * v + 2] * d.z);
-}
-
 // Nothing moves across this point: the compiler otherwise gathers loads that
 // are spread through the arithmetic on purpose, or starts the next face's
 // reads early, and at one wavefront per SIMD the registers they wait in are
@@ -466,7 +455,8 @@ struct GradWG {
     }
   }
 
-  // (a phase of the march that has nothing left to do: publish fills the ring)
+  // (the host emulations' step between publishing and the barrier: publish
+  // fills the ring itself, no kernel calls this)
   __host__ __device__ static void ring_late(const MarchArgs&, const TileMap&, const GState<T>&, int, int, double*) {}
 
   // Ring position r of layer k from the neighbour's state u (the plane's

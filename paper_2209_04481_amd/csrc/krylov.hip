@@ -4,7 +4,7 @@
 // atomics.
 //
 // What bounds it: memory.  On the 1.66M-cell shell (119 MB a vector) the two
-// passes over the basis run at 4.8 (dots) and 5.5 TB/s (update) against 5.1
+// passes over the basis run at 4.5 (dots) and 5.4 TB/s (update) against 5.1
 // for a copy; a GMRES(30) sweep of them takes 27 ms where one pass per basis
 // vector and projection took 44.  On small shells it was launches: a step
 // with basis size j took 2 (j + 1) + 3 of them and takes 4 now, 46 instead of
@@ -55,9 +55,9 @@ __device__ __forceinline__ const KrylovSys& system_of(const KrylovSys* sys, cons
 // and <V_i, V_j> (i < j).  With the preconditioner x = D^-1 V_j, so diag x is
 // V_j itself.  A tile's entries of V_{j+1} and V_j stay in registers while the
 // basis streams past, so the pass reads each basis vector once.  blockIdx.y
-// takes a group of `group` basis vectors (all of them when the blocks alone
-// fill the chip; smaller groups where a short vector would leave it idle: each
-// group forms V_{j+1}'s entries again, the first one stores them).
+// takes a group of `group` basis vectors, so that short vectors fill the chip
+// too: each group reads w, V_j and the diagonal and forms V_{j+1}'s entries
+// again, the first one stores them.
 __global__ __launch_bounds__(kT) void krylov_dots_kernel(const KrylovSys* __restrict__ sys,
                                                          const int32_t* __restrict__ owner, int j, int group) {
   __shared__ double acc[kWaves][2 * (kKrylovMaxM + 1)];
@@ -317,8 +317,10 @@ hipError_t launch_krylov_combine(const KrylovSys* sys, const KrylovOut* out, con
 
 hipError_t launch_krylov_step(const KrylovSys* sys, const int32_t* owner, int systems, int blocks, int m, int j,
                               hipStream_t s) {
-  // groups of basis vectors: none while the blocks themselves give every CU
-  // four (1,024), otherwise enough of them to reach that
+  // groups of basis vectors: enough of them that with the blocks every CU has
+  // four workgroups (1,024).  One system has at most kKrylovMaxBlocks blocks, so
+  // two groups or more; the ensemble's blocks, about 1,024, fall a little short
+  // of it and make two.
   int groups = (1024 + blocks - 1) / blocks;
   if (groups > j + 1) groups = j + 1;
   const int group = (j + 1 + groups - 1) / groups;

@@ -28,7 +28,7 @@
 // 13.3M cells, the pass 4.5, bound by its own arithmetic (about 6,000 vector
 // instructions a layer) and by LDS and dependent arithmetic with one wavefront
 // per SIMD.  With 54 stored face states it read 72 values a cell and took 5.3
-// ms.  The 13.3M-cell VJP takes 6.7 ms, the 1.66M-cell one 0.97; with every
+// ms.  The 13.3M-cell VJP takes 6.7 ms, the 1.66M-cell one 0.94; with every
 // contribution through memory (the cell-centric passes of cfv_vjp.hpp, kept
 // for the shells that fill tiles badly) 10.5 and 1.50.
 #include "cfv_adjmarch.hpp"
